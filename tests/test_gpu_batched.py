@@ -257,3 +257,29 @@ def test_default_variant_of_many_cuboids(per_cu, matrix, dt):
     Y = plan.run(*(dev(p[k], dt) for k in "XABC")).double().cpu().numpy()
     ref = oracle.batched(p["dims"], p["X"], p["A"], p["B"], p["C"])
     assert pins.rel_fro(Y, ref) <= (1e-5 if dt == torch.float32 else 1e-12)
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2, 3, 4])
+def test_infinite_values_stay_infinite(variant):
+    """With positive data a cuboid that holds an infinity (its last value, the
+    end of a fiber in each mode, or its first) is infinite throughout, none of
+    it NaN, and the others are what they are without it; sizes on either side
+    of the groups of four that the products take."""
+    dims = [(n, m, k, 3, 2, 5) for n in (1, 4, 5) for m in (2, 7, 8) for k in (3, 6, 13)] + [(16, 15, 9, 16, 1, 7)]
+    p = workloads.random_batched(dims, seed=43, dtype=np.float32)
+    for k in "XABC":
+        p[k] = np.abs(p[k]) + np.float32(0.1)
+    plan = BatchedPlan(p["dims"], dtype=torch.float32)
+    plan.set_config(64, 1, variant)
+    bufs = [dev(p[k], torch.float32) for k in "XABC"]
+    want = plan.run(*bufs).cpu().numpy()
+    X = p["X"].copy()
+    xo = np.cumsum([0] + [a * b * c for a, b, c, *_ in dims])
+    yo = np.cumsum([0] + [a * b * c for *_, a, b, c in dims])
+    hit = list(range(0, len(dims), 2))
+    for i, k in enumerate(hit):
+        X[xo[k + 1] - 1 if i % 2 == 0 else xo[k]] = np.inf
+    Y = plan.run(dev(X, torch.float32), *bufs[1:]).cpu().numpy()
+    for k in range(len(dims)):
+        got = Y[yo[k]:yo[k + 1]]
+        assert np.all(got == np.inf) if k in hit else np.array_equal(got, want[yo[k]:yo[k + 1]]), (k, dims[k], got)
