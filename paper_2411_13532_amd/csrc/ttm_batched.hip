@@ -880,14 +880,9 @@ int ttm_chain_batched_loop(const ttm_batched_plan *p, const void *X, const void 
     for (int64_t k = 0; k < p->count; ++k) {
         a.desc = p->d_desc + k;
         const bool f64 = p->dtype == TTM_F64;
-        if (f64)
-            hipLaunchKernelGGL((k_batched<double, 1>), dim3(1), dim3(64), lds, st, a, static_cast<const double *>(X),
-                               static_cast<const double *>(A), static_cast<const double *>(B),
-                               static_cast<const double *>(C), static_cast<double *>(Y));
-        else
-            hipLaunchKernelGGL((k_batched<float, 2>), dim3(1), dim3(64), lds, st, a, static_cast<const float *>(X),
-                               static_cast<const float *>(A), static_cast<const float *>(B),
-                               static_cast<const float *>(C), static_cast<float *>(Y));
+        // a variant of the plan's family (vector units or matrix cores): the same bits
+        if (f64) launch_variant<double>(0, dim3(1), dim3(64), lds, st, a, X, A, B, C, Y);
+        else launch_variant<float>(p->variant < 3 ? 0 : 3, dim3(1), dim3(64), lds, st, a, X, A, B, C, Y);
         if (hipGetLastError() != hipSuccess) return TTM_ERR_HIP;
     }
     return TTM_OK;

@@ -283,3 +283,14 @@ def test_infinite_values_stay_infinite(variant):
     for k in range(len(dims)):
         got = Y[yo[k]:yo[k + 1]]
         assert np.all(got == np.inf) if k in hit else np.array_equal(got, want[yo[k]:yo[k + 1]]), (k, dims[k], got)
+
+
+def test_launch_loop_matches_the_default_of_many_cuboids():
+    """One launch per cuboid takes the plan's family of variants: the same bits
+    as the persistent launch, also where the default is a matrix-core one."""
+    count = 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    p = workloads.random_batched(ragged_dims(np.random.default_rng(44), count, 1, 6), seed=45, dtype=np.float32)
+    plan = BatchedPlan(p["dims"], dtype=torch.float32)
+    assert plan.config()["variant"] == 4
+    bufs = [dev(p[k], torch.float32) for k in "XABC"]
+    assert torch.equal(plan.run(*bufs, mode="loop"), plan.run(*bufs))
