@@ -291,11 +291,12 @@ int ttm_batched_plan_set_config(ttm_batched_plan *plan, int threads, int blocks_
  * two cyclic first-order operators whose inverses are recursions that forget
  * their start after K points (the diagonal dominance of Sec. 4.2), so each
  * point is read once and written once; the result equals the exact solve up to
- * rounding, and a NaN or infinity in X spoils the points within about 2 K of
- * it.  Other alpha take the periodic Thomas algorithm (forward and backward
- * sweeps through Y), where one spoils its fiber.  The paper's values are
- * alpha = 1/3,
- * a = 14/9, b = 1/9.
+ * rounding.  A NaN or infinity in X spoils the points within K + 40 of it, or,
+ * along modes 1 and 2 of fields whose planes lie 512 KiB and more apart, those
+ * from K + 10 before it to the fiber's end, and its whole fiber from the last
+ * K + 2 points.  Other alpha take the periodic Thomas algorithm (forward and
+ * backward sweeps through Y), where one spoils its fiber.  The paper's values
+ * are alpha = 1/3, a = 14/9, b = 1/9.
  */
 typedef struct {
     double alpha, a, b, h;   /* |alpha| < 1/2 (diagonal dominance); h != 0 */

@@ -408,12 +408,15 @@ __global__ void __launch_bounds__(256) k_compact_rows_full(const CompactArgs a, 
 // than K is gone round as often as K points take), and the thread runs its
 // recursion again from it.  The same backwards.  Each point is read once and
 // written once, whatever n.  Fibers too long for one block are taken in chunks
-// with K points more at either end, from zero there.
+// with K + 2 points more at either end, from zero there; the right-hand side is
+// zero at a chunk's two outermost points, whose neighbours it does not hold, so
+// that nothing of one end reaches the other.
 // ---------------------------------------------------------------------------
 struct SegArgs {
     int64_t n, stride, nfib, i3, s12, groups;
     int mode, S, q, r, H;        // segments; the first r hold q + 1 points, the others q; segments to look back over
-    int nchunk, M, K;            // nchunk > 1: chunks of M outputs, S q = M + 2 K points read for each (r = 0)
+    int K;                       // points a recursion remembers
+    int nchunk, M, pad;          // nchunk > 1: chunks of M outputs, S q = M + 2 pad points read for each (r = 0)
     int block;                   // modes 1, 2: 2^block fibers in a block; mode 3: rows in a block
     double ca, cb, rho, scale;   // a / (2h), b / (4h), rho, 1 + rho^2
     double mq, mq1;              // (-rho)^q, (-rho)^(q + 1)
@@ -518,8 +521,8 @@ __global__ void __launch_bounds__(1024) k_compact_lines(const SegArgs a, const T
                 base = (f / a.i3) * a.s12 + f % a.i3;
             }
         }
-        // first point of the segment; in chunks modulo n (M + 2 K points may go round)
-        const int64_t j0 = chunk * a.M - (a.nchunk > 1 ? a.K : 0) + int64_t(sg) * a.q + (sg < a.r ? sg : a.r);
+        // first point of the segment; in chunks modulo n (M + 2 pad points may go round)
+        const int64_t j0 = chunk * a.M - (a.nchunk > 1 ? a.pad : 0) + int64_t(sg) * a.q + (sg < a.r ? sg : a.r);
         T u[C + 4];
         if (live) {
             if (a.nchunk == 1) {
@@ -552,6 +555,8 @@ __global__ void __launch_bounds__(1024) k_compact_lines(const SegArgs a, const T
             u[C + 3] = n1;
 #pragma unroll
             for (int i = 0; i < C; ++i) v[i] = ca * (u[i + 3] - u[i + 1]) + cb * (u[i + 4] - u[i]);
+            if (a.nchunk > 1 && sg == 0) v[0] = v[1] = T(0);
+            if (a.nchunk > 1 && sg == a.S - 1) v[C - 1] = v[C - 2] = T(0);
         } else {
 #pragma unroll
             for (int i = 0; i < C; ++i) v[i] = T(0);
@@ -606,7 +611,7 @@ __global__ void __launch_bounds__(1024) k_compact_rows1p(const SegArgs a, const 
         T *dst = Y + r0 * a.n;
         const int have = rows * width;
         if (a.nchunk > 1) {
-            const int64_t c0 = chunk * a.M - a.K;
+            const int64_t c0 = chunk * a.M - a.pad;
             for (int k = tid; k < width; k += nt) {
                 int64_t j = (c0 + k) % a.n;
                 if (j < 0) j += a.n;
@@ -644,6 +649,8 @@ __global__ void __launch_bounds__(1024) k_compact_rows1p(const SegArgs a, const 
             u[C + 3] = n1;
 #pragma unroll
             for (int i = 0; i < C; ++i) v[i] = ca * (u[i + 3] - u[i + 1]) + cb * (u[i + 4] - u[i]);
+            if (a.nchunk > 1 && sg == 0) v[0] = v[1] = T(0);
+            if (a.nchunk > 1 && sg == a.S - 1) v[C - 1] = v[C - 2] = T(0);
         } else {
 #pragma unroll
             for (int i = 0; i < C; ++i) v[i] = T(0);
@@ -658,7 +665,7 @@ __global__ void __launch_bounds__(1024) k_compact_rows1p(const SegArgs a, const 
         __syncthreads();
         if (a.nchunk > 1) {
             const int64_t lo = chunk * a.M, hi = lo + a.M < a.n ? lo + a.M : a.n;
-            for (int k = tid; k < int(hi - lo); k += nt) dst[lo + k] = ub[pos(k + a.K)];
+            for (int k = tid; k < int(hi - lo); k += nt) dst[lo + k] = ub[pos(k + a.pad)];
         } else if (VEC) {
             for (int k = tid * VE; k < have; k += nt * VE) {
                 if (k + VE <= have) {
@@ -805,7 +812,8 @@ int single_pass(const SegArgs &in, const T *X, T *Y, hipStream_t st) {
     a.nchunk = 1;
     if (S > most) {
         S = most;
-        a.M = int(S) * C - 2 * a.K;
+        a.pad = a.K + 2;
+        a.M = int(S) * C - 2 * a.pad;
         a.nchunk = int(ceil_div(a.n, a.M));
         a.q = C;
     } else {

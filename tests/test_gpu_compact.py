@@ -192,3 +192,35 @@ def test_compact_exact_sweeps_match_oracle(shape, dt):
             Y, Xd = gpu_apply(X, mode, 0.49, A, B, 0.01, dt)
             ref = oracle.compact6_apply(Xd.double().cpu().numpy(), mode, 0.49, A, B, 0.01)
             assert pins.rel_fro(Y, ref) <= 20 * TOL[dt], mode
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("mode,n", [(1, 2050), (2, 2050), (3, 8193), (3, 20000), (2, 300)])
+def test_compact_a_value_reaches_no_further_than_the_recursions(mode, n, dt):
+    """A NaN spoils the points within K + 40 of it (K = 39 in float64, 19 in
+    float32) and no others, a large value adds nothing past them: also where a
+    fiber is taken in chunks, whose two ends are no neighbours."""
+    reach = (39 if dt == torch.float64 else 19) + 40
+    shape = [2, 2]
+    shape.insert(mode - 1, n)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    X = torch.randn(shape, generator=g, device=DEV, dtype=dt)
+    h = 1.0
+    want = compact_apply(X, mode, h=h)
+    at = torch.arange(n, device=DEV)
+    big, tol = (1e12, 1e-12) if dt == torch.float64 else (1e6, 2e-6)
+    # (a chunk of 1024 or 8192 points ends K to K + 2 points past its outputs)
+    ends = [e - 1 - k for e in (1024, 8192) for k in range(18, 42)]
+    for p in [q for q in [0, 511, 930, 1023, *ends, n - 40, n - 20, n - 1] if 0 <= q < n]:
+        d = (at - p).abs()
+        far = torch.minimum(d, n - d) > reach
+        X1 = X.clone()
+        X1.select(mode - 1, p).fill_(float("nan"))
+        Y = compact_apply(X1, mode, h=h).movedim(mode - 1, 0)
+        assert not torch.isnan(Y[far]).any(), (p, at[torch.isnan(Y).flatten(1).any(1)])
+        assert torch.isnan(Y[(p + 1) % n]).all()
+        X1.select(mode - 1, p).fill_(big)
+        Y = compact_apply(X1, mode, h=h).movedim(mode - 1, 0)
+        diff = (Y - want.movedim(mode - 1, 0))[far].abs().max() / want.abs().max()
+        assert float(diff) <= tol, (p, float(diff))
