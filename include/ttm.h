@@ -284,8 +284,8 @@ int ttm_batched_plan_set_config(ttm_batched_plan *plan, int threads, int blocks_
  * Y = X x_mode D with D = A_c^-1 B_c (A_c the cyclic tridiagonal left side,
  * B_c the cyclic five-point right side), evaluated without forming D: the
  * right-hand side is built on the fly and the cyclic tridiagonal system
- * (Sec. 2.1) is solved in one of two ways.  With rho = (1 - sqrt(1 - 4
- * alpha^2)) / (2 alpha) (alpha = 1/3 gives 0.382), coefficients alpha for which
+ * (Sec. 2.1) is solved in one of two ways.  With rho = 2 alpha / (1 + sqrt(1
+ * - 4 alpha^2)) (alpha = 1/3 gives 0.382), coefficients alpha for which
  * rho^K is below half the rounding unit for some K <= 64 (|alpha| up to about
  * 0.42 in F64 and 0.48 in F32) take a single pass: A_c factors as a product of
  * two cyclic first-order operators whose inverses are recursions that forget

@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(256) k_compact_rows_full(const CompactArgs a, 
 // ---------------------------------------------------------------------------
 // Single-pass sweep.  A_c = tridiag(alpha, 1, alpha) with periodic corners is
 // circulant and, for |alpha| < 1/2, factors as
-//     A_c = c (I + rho S)(I + rho S^T),  rho = (1 - sqrt(1 - 4 alpha^2)) / (2 alpha),
+//     A_c = c (I + rho S)(I + rho S^T),  rho = 2 alpha / (1 + sqrt(1 - 4 alpha^2)),
 //     c = 1 / (1 + rho^2),  (S y)_j = y_{j+1} (indices mod n),
 // so A_c y = d is a cyclic forward recursion f_j = d_j - rho f_{j-1} followed
 // by a cyclic backward recursion g_j = f_j - rho g_{j+1}, y = (1 + rho^2) g.
@@ -923,7 +923,9 @@ int ttm_compact_apply(const int64_t *dims, int mode, const void *X, void *Y, int
     // left, takes the same path as that call, and nothing has to be prepared
     // for the single pass.
     const double alpha = coef->alpha;
-    const double rho = alpha == 0.0 ? 0.0 : (1.0 - sqrt(1.0 - 4.0 * alpha * alpha)) / (2.0 * alpha);
+    // (the other form of the root, (1 - sqrt(1 - 4 alpha^2)) / (2 alpha), loses
+    // its digits to cancellation where alpha is small)
+    const double rho = 2.0 * alpha / (1.0 + sqrt(1.0 - 4.0 * alpha * alpha));
     if (const int K = seg_memory(rho, dtype)) {
         SegArgs sa{};
         sa.n = n;

@@ -224,3 +224,14 @@ def test_compact_a_value_reaches_no_further_than_the_recursions(mode, n, dt):
         Y = compact_apply(X1, mode, h=h).movedim(mode - 1, 0)
         diff = (Y - want.movedim(mode - 1, 0))[far].abs().max() / want.abs().max()
         assert float(diff) <= tol, (p, float(diff))
+
+
+@pytest.mark.parametrize("alpha", [1e-8, -1e-6, 1e-5, 1e-3, 0.01])
+def test_compact_small_alpha(alpha):
+    """A nearly explicit scheme: rho = alpha + O(alpha^3) has all its digits (the
+    bound: some tens of roundings a point, of a solve with condition number 1)."""
+    X = np.random.default_rng(18).standard_normal((48, 40, 50))
+    for mode in (1, 2, 3):
+        Y, _ = gpu_apply(X, mode, alpha, A, B, 0.01)
+        ref = oracle.compact6_apply(X, mode, alpha, A, B, 0.01)
+        assert pins.rel_fro(Y, ref) <= 1e-14, (mode, alpha, pins.rel_fro(Y, ref))
