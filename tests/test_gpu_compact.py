@@ -235,3 +235,21 @@ def test_compact_small_alpha(alpha):
         Y, _ = gpu_apply(X, mode, alpha, A, B, 0.01)
         ref = oracle.compact6_apply(X, mode, alpha, A, B, 0.01)
         assert pins.rel_fro(Y, ref) <= 1e-14, (mode, alpha, pins.rel_fro(Y, ref))
+
+
+# The single pass up to its longest memory (K = 64), short fibers gone round
+# several times by it, and alpha on both sides of the change to the sweeps.
+@pytest.mark.parametrize("dt,alpha", [(torch.float64, a) for a in (0.25, 0.42, -0.42, 0.425)] +
+                         [(torch.float32, a) for a in (0.42, 0.45, -0.45, 0.48, -0.48, 0.485)],
+                         ids=lambda v: str(v).replace("torch.", ""))
+@pytest.mark.parametrize("n", [3, 4, 5, 17, 41, 210, 1025, 2050, 8193])
+def test_compact_alphas_near_the_change_of_solver(n, dt, alpha):
+    """Tolerance by the solve's condition number, 5 at alpha = 1/3."""
+    tol = TOL[dt] * max(1.0, (1 + 2 * abs(alpha)) / (1 - 2 * abs(alpha)) / 5)
+    X = np.random.default_rng(n + 7).standard_normal((3, 5, n))
+    for mode in (1, 2, 3) if n < 8000 else (3,):
+        Y, Xd = gpu_apply(np.moveaxis(X, 2, mode - 1), mode, alpha, A, B, 2 * np.pi / n, dt)
+        ref = oracle.compact6_apply(Xd.double().cpu().numpy(), mode, alpha, A, B, 2 * np.pi / n)
+        err = pins.rel_fro(Y, ref)
+        print(f"[compact {dt} alpha {alpha} n {n} mode {mode}] rel err {err:.3e}", flush=True)
+        assert err <= tol, (mode, err, tol)
