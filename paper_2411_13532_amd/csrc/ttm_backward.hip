@@ -44,6 +44,7 @@ struct BwdPlan {
 };
 
 constexpr int64_t KT_F32 = 32, KT_F64 = 16;
+constexpr int SK_WAVES = 4;   // waves of a streaming kernel's workgroup (but dC's)
 
 struct SplitK {
     int ks;
@@ -74,8 +75,11 @@ void make_bwd_plan(const ttm_shape &s, int math, bool dX, bool dA, bool dB, bool
     p.need_r = dX || dC;
     const int64_t KT = math == TTM_MATH_F64 ? KT_F64 : KT_F32, VE = int64_t(16 / p.esz);
     const int64_t M = p.I1 * p.I2;
-    p.stream = p.J3 <= 64 && p.J3 >= VE && p.I3 >= VE && M < (int64_t(1) << 31) && p.I3 < (int64_t(1) << 24);
-    p.stream_vr = p.J3 <= 64 && p.J2 <= 64 && p.I2 >= VE && p.I2 < (int64_t(1) << 24) && p.I1 < (int64_t(1) << 31);
+    // (the column tiles of dX and dC, and R's row tiles, are grid y: at most
+    // 65535 of them; the general product has its tiles along grid x)
+    constexpr int64_t YMAX = 65535;
+    p.stream = p.J3 <= 64 && p.J3 >= VE && p.I3 >= VE && M < (int64_t(1) << 31) && ceil_div(p.I3, 64 * VE) <= YMAX;
+    p.stream_vr = p.J3 <= 64 && p.J2 <= 64 && p.I2 >= VE && ceil_div(p.I2, 32 * SK_WAVES) <= YMAX && p.I1 < (int64_t(1) << 31);
     // partials of the split contractions
     int64_t part[3] = {0, 0, 0};
     if (dA) {
@@ -145,8 +149,6 @@ GemmArgs gargs() {
 // W 47.8, now 25.9 us; dX 35.0, now 17.5; dC 33.6, now 16.6; V 16.0, now 9.9;
 // R 12.7, now 8.7.
 // ---------------------------------------------------------------------------
-constexpr int SK_WAVES = 4;
-
 template <typename T> struct Sk;
 template <> struct Sk<float> {
     typedef f32x4 acc;

@@ -191,3 +191,27 @@ def test_streaming_kernels_vs_oracle(shape, math, tol):
     for k in range(4):
         alone = chain_backward(*args, math=math, need=[i == k for i in range(4)])[k]
         assert torch.equal(alone, got[k]), k
+
+
+@pytest.mark.parametrize("I,J,dt", [((1, 65535 * 128, 4), (1, 2, 4), torch.float32), ((1, 65535 * 128 + 1, 4), (1, 2, 4), torch.float32),
+                                    ((2, 2, 65535 * 128 + 2), (1, 1, 4), torch.float64), ((2, 4, 65535 * 128), (2, 3, 2), torch.float64)],
+                         ids=lambda v: str(v).replace("torch.", ""))
+def test_backward_of_one_very_long_mode(I, J, dt):
+    """The last size whose tiles fit the y grid of a launch and the first past it."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    X, G, A, B, C = (torch.randn(s, generator=g, device=DEV, dtype=dt) for s in (I, J, *((J[n], I[n]) for n in range(3))))
+    got = chain_backward(G, X, A, B, C, math="f64" if dt == torch.float64 else "f32")
+    Xd, Gd, Ad, Bd, Cd = (t.double() for t in (X, G, A, B, C))
+    mul = lambda T, M, n: torch.tensordot(T, M, dims=([n], [1])).movedim(-1, n)     # T x_{n+1} M
+    W = mul(Xd, Cd, 2)
+    H = mul(Gd, Ad.t(), 0)
+    R = mul(H, Bd.t(), 1)
+    want = (mul(R, Cd.t(), 2), torch.tensordot(Gd, mul(W, Bd, 1), dims=([1, 2], [1, 2])),
+            torch.tensordot(H, W, dims=([0, 2], [0, 2])), torch.tensordot(R, Xd, dims=([0, 1], [0, 1])))
+    # sums of up to max(I) random terms in one chain: about half a rounding unit times the root of their number
+    tol = (2.0 ** -53 if dt == torch.float64 else 2.0 ** -24) * max(I) ** 0.5
+    for name, a, b in zip(("dX", "dA", "dB", "dC"), got, want):
+        err = float((a.double() - b).norm() / b.norm())
+        print(f"[one long mode {I} {name}] rel err {err:.3e}, bound {tol:.1e}", flush=True)
+        assert err <= tol, (name, err)
