@@ -404,9 +404,11 @@ __global__ void __launch_bounds__(256) k_compact_rows_full(const CompactArgs a, 
 // the value that enters segment l is then
 //     e_{l-1} + m_{l-1} (e_{l-2} + m_{l-2} (e_{l-3} + ...)),
 // e the segments' end values and m = (-rho)^length their multipliers, over the
-// H segments that hold the last K points (modulo the fiber: a fiber shorter
-// than K is gone round as often as K points take), and the thread runs its
-// recursion again from it.  The same backwards.  Each point is read once and
+// H segments that hold the last K points, and the thread runs its recursion
+// again from it.  Where those are the whole fiber, one turn is enough: further
+// ones multiply its sum by 1 / (1 - (-rho)^n).  (Gone round as often as K points
+// take, fibers of 5 and 6 points paid for 40 dependent LDS reads: 267 x 5 x 1200
+// in double along mode 2 15.5 us, now 8.5; the exact sweeps, prepared, 7.8.)  The same backwards.  Each point is read once and
 // written once, whatever n.  Fibers too long for one block are taken in chunks
 // with K + 2 points more at either end, from zero there; the right-hand side is
 // zero at a chunk's two outermost points, whose neighbours it does not hold, so
@@ -420,6 +422,7 @@ struct SegArgs {
     int block;                   // modes 1, 2: 2^block fibers in a block; mode 3: rows in a block
     double ca, cb, rho, scale;   // a / (2h), b / (4h), rho, 1 + rho^2
     double mq, mq1;              // (-rho)^q, (-rho)^(q + 1)
+    double turns;                // H == S: 1 / (1 - (-rho)^n), else 1
 };
 
 // The two recursions over the thread's points, d -> y, in place: v[0 .. C), or
@@ -429,7 +432,7 @@ struct SegArgs {
 template <typename T, int C>
 __device__ __forceinline__ void seg_solve(const SegArgs &a, T (&v)[C], bool lng, int sg, bool live, T *e, T *eb, int shift,
                                           int at) {
-    const T rho = T(a.rho), mq = T(a.mq), mq1 = T(a.mq1);
+    const T rho = T(a.rho), mq = T(a.mq), mq1 = T(a.mq1), turns = T(a.turns);
     T f = T(0);
 #pragma unroll
     for (int i = 0; i < C - 1; ++i) f = v[i] - rho * f;
@@ -440,13 +443,13 @@ __device__ __forceinline__ void seg_solve(const SegArgs &a, T (&v)[C], bool lng,
     f = T(0);
     if (live) {
         int g = sg - a.H;
-        if (a.nchunk > 1) g = g < 0 ? 0 : g;
-        else if (g < 0) g = (g % a.S + a.S) % a.S;
+        if (g < 0) g = a.nchunk > 1 ? 0 : g + a.S;
         const int steps = a.nchunk > 1 ? sg - g : a.H;
         for (int m = 0; m < steps; ++m) {
             f = e[(g << shift) + at] + (g < a.r ? mq1 : mq) * f;
             g = g + 1 == a.S ? 0 : g + 1;
         }
+        f *= turns;
     }
 #pragma unroll
     for (int i = 0; i < C; ++i) {
@@ -461,13 +464,13 @@ __device__ __forceinline__ void seg_solve(const SegArgs &a, T (&v)[C], bool lng,
     f = T(0);
     if (live) {
         int g = sg + a.H;
-        if (a.nchunk > 1) g = g >= a.S ? a.S - 1 : g;
-        else if (g >= a.S) g %= a.S;
+        if (g >= a.S) g = a.nchunk > 1 ? a.S - 1 : g - a.S;
         const int steps = a.nchunk > 1 ? g - sg : a.H;
         for (int m = 0; m < steps; ++m) {
             f = eb[(g << shift) + at] + (g < a.r ? mq1 : mq) * f;
             g = g == 0 ? a.S - 1 : g - 1;
         }
+        f *= turns;
     }
     const T scale = T(a.scale);
     if (lng) {
@@ -822,6 +825,11 @@ int single_pass(const SegArgs &in, const T *X, T *Y, hipStream_t st) {
     }
     a.S = int(S);
     a.H = int(ceil_div(a.K, a.q));
+    a.turns = 1.0;
+    if (a.nchunk == 1 && a.H >= a.S) {
+        a.H = a.S;
+        a.turns = 1.0 / (1.0 - pow(-a.rho, double(a.n)));
+    }
     a.mq = pow(-a.rho, double(a.q));
     a.mq1 = pow(-a.rho, double(a.q + 1));
     size_t lds;
