@@ -224,6 +224,16 @@ constexpr SlabTile slab_tile(int math, bool x_float, int CB) {
     t.lds = 2 * t.slot + (t.walias ? 0 : t.wb * (x3 ? 2 : 1));
     return t;
 }
+// Resident waves per SIMD the kernel's registers are cut for: as many as its
+// tile has room for (without the bound the allocator gave up a wave for a few
+// values more: 512^3 -> 64 in float 126 registers, or 145).
+constexpr int slab_waves(int math, bool x_float, int CB, int JB) {
+    if (JB == 8 || math == M_BF16X3) return math == M_F32 && CB <= 4 ? 3 : 2;
+    if (math == M_F32) return CB == 1 ? 5 : CB <= 4 || (!x_float && JB == 1) ? 4 : 3;
+    if (math == M_F64) return CB <= 2 || JB <= 2 ? 3 : 2;
+    if (!x_float && CB == 2 && JB <= 2) return 4;
+    return CB <= 2 || CB == 8 || (x_float ? CB == 6 || (CB == 3 && JB == 1) : CB <= 4) ? 3 : 2;
+}
 // A group loaded from `off`, or from the tensor's last whole group where it
 // would end past it, with its first n values in place and zeros after them.
 // (A tensor shorter than a group was not loaded at all: value by value here.)
@@ -349,7 +359,7 @@ __device__ __forceinline__ void slab_mode2(typename MathTraits<MATH>::accv_t (&v
 // 181 x 210 x 155 -> 24 x 30 x 41 in double 59 us, now 45 us;
 // 332 x 409 x 232 -> 65 x 80 x 48 in double 568 us, now 224 us.
 template <int MATH, typename XT, int CB, int JB>
-__global__ void __launch_bounds__(SLAB_THREADS, 2) k_slab(const SlabArgs a) {
+__global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT, float>::value, CB, JB)) k_slab(const SlabArgs a) {
     typedef SlabCfg<MATH, XT, CB> CF;
     typedef typename CF::TR TR;
     typedef typename CF::LT LT;
@@ -562,7 +572,22 @@ __global__ void __launch_bounds__(SLAB_THREADS, 2) k_slab(const SlabArgs a) {
                 }
         }
     };
-    auto mode2 = [&](int slot) __attribute__((always_inline)) {
+    auto mode2 = [&](int64_t t, int slot) __attribute__((always_inline)) {
+        // rows past the range, in the wave that the range ends in: X's zeros
+        // times an infinite entry of C are NaN, which B's zeros would pass on
+        // to every j2 (later waves have formed no products; in bf16 below, as
+        // the values are packed; a split infinity is NaN by itself)
+        const int live = int(row_end - row_begin - t * TM) - wave * (16 * MB);
+        if (RAW && live > 0 && live < 16 * MB) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool in = mb * 16 + TR::acc_row(g, r) < live;
+#pragma unroll
+                    for (int nb = 0; nb < CB; ++nb) wacc[mb][nb][r] = in ? wacc[mb][nb][r] : acc_t(0);
+                }
+        }
         unsigned char *wh = smem + (CF::WALIAS ? slot * CF::SLOT : 2 * CF::SLOT), *wl = wh + CF::WB;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -584,8 +609,9 @@ __global__ void __launch_bounds__(SLAB_THREADS, 2) k_slab(const SlabArgs a) {
                         bf16_split2(w[2], w[3], h1, l1);
                         *reinterpret_cast<u32x2 *>(wl + off + pos) = u32x2{l0, l1};
                     } else {
-                        h0 = cvt_pk_bf16(w[0], w[1]);
-                        h1 = cvt_pk_bf16(w[2], w[3]);
+                        const int n = live - mb * 16 - 4 * g;
+                        h0 = cvt_pk_bf16(w[0], w[1]) & (n >= 2 ? ~0u : n == 1 ? 0xffffu : 0u);
+                        h1 = cvt_pk_bf16(w[2], w[3]) & (n >= 4 ? ~0u : n == 3 ? 0xffffu : 0u);
                     }
                     *reinterpret_cast<u32x2 *>(wh + off + pos) = u32x2{h0, h1};
                 }
@@ -671,7 +697,7 @@ __global__ void __launch_bounds__(SLAB_THREADS, 2) k_slab(const SlabArgs a) {
         __syncthreads();
         if (kc == nk - 1) {
             place_b(t);
-            mode2(S);
+            mode2(t, S);
         }
         t = t1; kc = kc1;
         t1 = t2; kc1 = kc2;
