@@ -153,10 +153,11 @@ int ttm_chain(const ttm_shape *shape,
  *
  * Scratch: TTM_NOALLOC_SCRATCH_BYTES bytes of device memory per GPU, part of
  * the library's device code (it exists on a GPU once the library's kernels
- * are loaded there, and is held until the process ends).  Shapes whose
- * ttm_chain_workspace_size exceeds it return TTM_ERR_WORKSPACE (the
- * 1024^3 -> 128^3 bf16x3 chain needs about 82 MiB and must use ttm_chain;
- * 512^3 -> 64^3 fits).  The first call on a GPU looks up the array's device
+ * are loaded there, and is held until the process ends).  Shapes that need
+ * more of it return TTM_ERR_WORKSPACE (ttm_chain_workspace_size is an upper
+ * bound of the need: it covers every slab-kernel selection; the 1024^3 -> 128^3
+ * bf16x3 chain needs about 82 MiB and must use ttm_chain; 512^3 -> 64^3 fits).
+ * The first call on a GPU looks up the array's device
  * address (no allocation); make that first call outside graph capture.
  *
  * Every call on one GPU uses the same scratch: calls that overlap in time on

@@ -1991,7 +1991,8 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
     p.ldb = round_up(I2, SLAB_TM);
     p.lda = round_up(I1, KC);
 
-    for (bool one_split = false, tight = false;; ) {
+    ChainPlan first;
+    for (bool reduced = false, one_split = false, tight = false;; ) {
         p.S = int(ceil_div(I2, p.rows_per_split));
         p.P = p.S * p.WR;
         // mode-1 kernel: split the i1 range while the column tiles alone leave the
@@ -2034,8 +2035,14 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         p.total = off;
         // the library-owned scratch holds what it holds with one row split, one
         // mode-1 split and tiles of at most 64 rows j2 and 64 columns j3 (which
-        // pad J2 and J3 least): splits and tiles that pass it are taken back
+        // pad J2 and J3 least): splits and tiles that pass it are taken back,
+        // unless even those do (ttm_chain then loses by fewer: bf16x3 1024 x 512 x
+        // 771 -> 128 897 us with one split and small tiles, 525 as first planned)
         if (p.kern != SLAB_REG || math == TTM_MATH_BF16 || p.total <= TTM_NOALLOC_SCRATCH_BYTES) break;
+        if (!reduced) {
+            first = p;
+            reduced = true;
+        }
         if (p.S > 1) {
             p.rows_per_split = round_up(ceil_div(I2, p.S / 2), rt.TM);
         } else if (!one_split && p.KS > 1) {
@@ -2049,6 +2056,7 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
             rt = slab_tile(math, xdt != TTM_BF16, p.CB);
             p.rows_per_split = round_up(I2, rt.TM);
         } else {
+            p = first;
             break;
         }
     }

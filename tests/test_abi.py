@@ -281,3 +281,20 @@ def test_noalloc_takes_shapes_up_to_its_scratch(lib, I, J, x, math):
 
     assert call(_lib.shape(I, J)) == _lib.TTM_ERR_HIP
     assert call(_lib.shape((I[0] * 8, *I[1:]), J)) == _lib.TTM_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("I,J,x,math", [((1024, 512, 771), (128, 128, 128), _lib.TTM_BF16, "bf16x3"),
+                                        ((2200, 512, 500), (128, 128, 128), _lib.TTM_F32, "f32"),
+                                        ((1024, 512, 500), (128, 128, 128), _lib.TTM_F64, "f64")],
+                         ids=["bf16x3", "f32", "f64"])
+def test_splits_are_kept_where_no_choice_fits_the_scratch(lib, I, J, x, math):
+    """Splits are taken back so that a call fits the library-owned scratch, and
+    only where it then does: the workspace beside V (J2 and J3 need no padding
+    here) is no smaller past the scratch than at half the size, which fits."""
+    esz = 8 if math == "f64" else 4
+
+    def beside_v(n):
+        return lib.ttm_chain_workspace_size(shp((n, *I[1:]), J), x, _lib.MATH[math]) - n * J[1] * J[2] * esz
+
+    assert beside_v(I[0]) + I[0] * J[1] * J[2] * esz > _lib.TTM_NOALLOC_SCRATCH_BYTES
+    assert beside_v(I[0]) >= beside_v(I[0] // 2)
