@@ -1871,6 +1871,8 @@ static bool combo_ok(int x, int f, int y, int m) {
 // V up to here goes to k_mode1_small (the figures at both ends are there)
 constexpr int64_t M1_SMALL_V = int64_t(24) << 20;
 
+constexpr int64_t GRID_YZ = 65535;   // workgroups of a launch along y and z
+
 // The direct-to-LDS kernel that takes a shape under the selection `mode`
 // (SLAB_REG: none).  Both need 16-byte aligned rows and whole chunks along i3:
 // k_slab_dma (256-byte chunks) X already in the operand format, k_slab_lc
@@ -1938,6 +1940,10 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         p.J2pad = p.n_j2_tiles * p.JB * 16;
     };
     tile();
+    const int64_t J1b = ceil_div(J1, 16);
+    // J within the grids of these tiles and of k_mode1's (where a tiling chosen
+    // below is finer, mode 1 keeps k_mode1 and the slab kernel takes another launch)
+    if (p.n_j3_tiles > GRID_YZ || p.n_j2_tiles > GRID_YZ || ceil_div(J1b, J1b >= 5 ? 8 : 4) > GRID_YZ) return false;
 
     // split the i2 rows of a slab so the grid has enough workgroups.  (Five to
     // seven j2 blocks count as two tiles of four, as they were once taken: the
@@ -1986,7 +1992,6 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         }
     }
 
-    const int64_t J1b = ceil_div(J1, 16);
     p.ldc = round_up(I3, KC);
     p.ldb = round_up(I2, SLAB_TM);
     p.lda = round_up(I1, KC);
@@ -2002,7 +2007,7 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         const int64_t NN = p.J2pad * p.J3pad;
         // mode-1 kernel tiling: MW row blocks and NW column blocks per wave;
         // V of at most SMALL_V bytes goes to the kernel that needs no split
-        p.m1_small = I1 * p.P * NN * int64_t(p.acc_sz) <= M1_SMALL_V;
+        p.m1_small = I1 * p.P * NN * int64_t(p.acc_sz) <= M1_SMALL_V && ceil_div(J1b, 4) <= GRID_YZ;
         if (p.m1_small) { p.m1_NW = 0; p.m1_MW = J1b > 2 ? 4 : int(J1b); }
         else if (J1b <= 2) { p.m1_NW = 1; p.m1_MW = int(J1b); }
         else { p.m1_NW = 4; p.m1_MW = J1b >= 5 ? 2 : 1; }
@@ -2061,22 +2066,32 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         }
     }
     // launch-grid limits
-    if (I1 * p.S > 0x7fffffffLL || p.n_j3_tiles > 65535 || p.n_j2_tiles > 65535 || p.n_m1_tiles > 65535 ||
-        p.J2pad * p.J3pad / 64 > 0x7fffffffLL || p.KS > 65535 || J1 * J2 > 0x7fffffffLL)
-        return false;
-    return true;
+    return I1 * p.S <= 0x7fffffffLL && p.n_j2_tiles <= GRID_YZ && p.J2pad * p.J3pad / 64 <= 0x7fffffffLL && J1 * J2 <= 0x7fffffffLL;
 }
 
 template <int MATH, typename XT, int CB, int JB>
 static int launch_slab(const ChainPlan &p, const SlabArgs &a, hipStream_t st) {
     typedef SlabCfg<MATH, XT, CB> CF;
-    dim3 grid(unsigned(a.I1 * a.S), unsigned(p.n_j3_tiles), unsigned(p.n_j2_tiles));
+    typedef typename CF::TR::fac_t FT;
+    typedef typename CF::TR::acc_t acc_t;
     static std::atomic<uint64_t> attr_set{0};
     if (int rc = ensure_lds_limit(reinterpret_cast<const void *>(&k_slab<MATH, XT, CB, JB>), CF::LDS, attr_set))
         return rc;
-    return launch("ttm_slab", st, [&] {
-        hipLaunchKernelGGL((k_slab<MATH, XT, CB, JB>), grid, dim3(SLAB_THREADS), CF::LDS, st, a);
-    });
+    // (more than one launch only for J3 in the millions)
+    for (int64_t t = 0; t < p.n_j3_tiles; t += GRID_YZ) {
+        SlabArgs b = a;
+        const int64_t col = t * CB * 16, coff = col * (MATH == M_F32 || MATH == M_F64 ? a.I3 : a.ldc);
+        b.Chi = static_cast<const FT *>(a.Chi) + coff;
+        b.Clo = a.Clo ? static_cast<const FT *>(a.Clo) + coff : nullptr;
+        b.V = static_cast<acc_t *>(a.V) + col;
+        b.J3 = a.J3 - col;
+        dim3 grid(unsigned(a.I1 * a.S), unsigned(std::min(p.n_j3_tiles - t, GRID_YZ)), unsigned(p.n_j2_tiles));
+        const int rc = launch("ttm_slab", st, [&] {
+            hipLaunchKernelGGL((k_slab<MATH, XT, CB, JB>), grid, dim3(SLAB_THREADS), CF::LDS, st, b);
+        });
+        if (rc) return rc;
+    }
+    return TTM_OK;
 }
 
 template <int MATH, typename XT, int CB>

@@ -298,3 +298,29 @@ def test_splits_are_kept_where_no_choice_fits_the_scratch(lib, I, J, x, math):
 
     assert beside_v(I[0]) + I[0] * J[1] * J[2] * esz > _lib.TTM_NOALLOC_SCRATCH_BYTES
     assert beside_v(I[0]) >= beside_v(I[0] // 2)
+
+
+# The longest factors in each arithmetic, and one past them.
+LONG_FACTORS = [((2, 3, 5), (65535 * 128, 2, 3), _lib.TTM_F64, "f64"), ((2, 3, 5), (65535 * 128, 2, 3), _lib.TTM_F32, "f32"),
+                ((2, 3, 5), (65535 * 128, 2, 3), _lib.TTM_BF16, "bf16"), ((2, 3, 5), (2, 65535 * 64, 3), _lib.TTM_F64, "f64"),
+                ((16, 3, 40), (2, 65535 * 128, 3), _lib.TTM_F32, "f32"), ((16, 3, 40), (2, 65535 * 128, 3), _lib.TTM_F32, "bf16x3"),
+                ((2, 3, 5), (2, 3, 65535 * 64), _lib.TTM_F64, "f64"), ((2, 3, 5), (2, 3, 65535 * 128), _lib.TTM_F32, "f32"),
+                ((2, 3, 5), (2, 3, 65535 * 128), _lib.TTM_F32, "bf16x3"), ((2, 3, 5), (2, 3, 65535 * 128), _lib.TTM_BF16, "bf16x3"),
+                ((2, 3, 5), (2, 3, 65535 * 128), _lib.TTM_F32, "bf16")]
+
+
+@pytest.mark.parametrize("I,J,x,math", LONG_FACTORS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_chain_takes_long_factors(lib, I, J, x, math):
+    """Without a device a call that passes every check fails at the device."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up addresses: only where nothing can be launched")
+    f = _lib.TTM_F64 if math == "f64" else _lib.TTM_F32
+    fake = [(k + 1) << 54 for k in range(6)]
+
+    def call(shape):
+        return lib.ttm_chain(ctypes.byref(shape), fake[0], x, fake[1], fake[2], fake[3], f, fake[4], f, _lib.MATH[math], fake[5], 1 << 50, None)
+
+    assert call(_lib.shape(I, J)) == _lib.TTM_ERR_HIP
+    assert lib.ttm_chain_workspace_size(shp(I, J), x, _lib.MATH[math]) > 0
+    assert call(_lib.shape(I, [j + (j > 3) for j in J])) == _lib.TTM_ERR_UNSUPPORTED
