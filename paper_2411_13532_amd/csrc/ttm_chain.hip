@@ -1868,7 +1868,13 @@ static bool combo_ok(int x, int f, int y, int m) {
     return false;
 }
 
-// V up to here goes to k_mode1_small (the figures at both ends are there)
+// V up to here, and few workgroups, go to k_mode1_small (the figures for V are
+// there): where the columns alone are many workgroups, k_mode1 needs no split
+// either and reads V 256 bytes a row.  Whole chains: 30 x 264 x 32 -> 64, 128, 512
+// in float (4096 workgroups) 74.5 us with k_mode1_small, 44.5 with k_mode1; 912 x
+// 100 x 30 -> 144, 16, 16 (48) 22.7, and 32 and more with the splits of k_mode1
+// and their sum.  Over 725 drawn chains the sides meet at about three workgroups
+// of eight waves a compute unit in float and double, two in the bf16 forms.
 constexpr int64_t M1_SMALL_V = int64_t(24) << 20;
 
 constexpr int64_t GRID_YZ = 65535;   // workgroups of a launch along y and z
@@ -2008,6 +2014,12 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         // mode-1 kernel tiling: MW row blocks and NW column blocks per wave;
         // V of at most SMALL_V bytes goes to the kernel that needs no split
         p.m1_small = I1 * p.P * NN * int64_t(p.acc_sz) <= M1_SMALL_V && ceil_div(J1b, 4) <= GRID_YZ;
+        const int64_t small_wg = NN / 16 * ceil_div(J1b, J1b > 2 ? 4 : J1b);
+        p.m1_small = p.m1_small && small_wg <= (bf ? 512 : 768);
+        // (plain bf16 with four partials and more in each of three and more
+        // rounds of the waves, and few rows: 960 x 200 x 16 -> 32, 16, 16 37.0 us
+        // with k_mode1_small, 29.1 with k_mode1 over fifteen splits)
+        if (math == TTM_MATH_BF16 && p.P >= 4 && I1 > 2 * 8 * KG && J1b <= 2) p.m1_small = false;
         if (p.m1_small) { p.m1_NW = 0; p.m1_MW = J1b > 2 ? 4 : int(J1b); }
         else if (J1b <= 2) { p.m1_NW = 1; p.m1_MW = int(J1b); }
         else { p.m1_NW = 4; p.m1_MW = J1b >= 5 ? 2 : 1; }
