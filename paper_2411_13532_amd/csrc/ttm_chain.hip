@@ -1872,8 +1872,7 @@ static bool combo_ok(int x, int f, int y, int m) {
 // there): where the columns alone are many workgroups, k_mode1 needs no split
 // either and reads V 256 bytes a row.  Whole chains: 30 x 264 x 32 -> 64, 128, 512
 // in float (4096 workgroups) 74.5 us with k_mode1_small, 44.5 with k_mode1; 912 x
-// 100 x 30 -> 144, 16, 16 (48) 22.7, and 32 and more with the splits of k_mode1
-// and their sum.  Over 725 drawn chains the sides meet at about three workgroups
+// 100 x 30 -> 144, 16, 16 (48) goes to it, 22.7.  Over 725 drawn chains the sides meet at about three workgroups
 // of eight waves a compute unit in float and double, two in the bf16 forms.
 constexpr int64_t M1_SMALL_V = int64_t(24) << 20;
 
@@ -1979,21 +1978,25 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         // row splits: a compute unit's workgroups n take n chunk times where
         // they fill it and about three where one waits out its chunk's trips
         // alone, for as many chunks as a workgroup has and four more for its
-        // start and end; and the partials of V are written and read (not for
-        // plain bf16, whose partials are fixed: SlabTile).
+        // start and end; and the partials of V are written and read, in units of
+        // the bytes of X that a chunk brings every compute unit (not for plain
+        // bf16, whose partials are fixed: SlabTile).  (As a share of X's bytes,
+        // which on a chip that is not full cost nothing, V kept 16 x 852 x 11 ->
+        // 140, 136, 39 in double to one split: 86.6 us, now 32.8.)
         // Counting rounds of workgroups alone (which took one split of 512 x 512 x
         // 500 -> 64 in float, and more than half of a second round idle) gave
         // 242 us there, this 215; 424 x 392 x 48 -> 8 x 15 x 16 in double 40.5 us
         // with its one split, 40.9 with this rule's two.
         const int64_t nk = ceil_div(I3, KC), occ = std::min(4, 163840 / rt.lds);
-        const double vx = 2.0 * double(p.J2pad * p.J3pad) * double(p.acc_sz) / (double(I2) * double(I3) * double(dtype_size(xdt)));
+        const double vx = 2.0 * double(I1) * double(p.J2pad) * double(p.J3pad) * double(p.acc_sz) /
+                          (256.0 * double(rt.TM * std::min<int64_t>(I3, KC)) * double(dtype_size(xdt)));
         double best = 0;
         const int64_t tiles = ceil_div(I2, rt.TM);
         for (int64_t c = 1; c <= std::min<int64_t>(tiles, 64) && math != TTM_MATH_BF16; c += c < 8 ? 1 : 8) {
             const int64_t per = ceil_div(tiles, c), wg = I1 * p.n_j3_tiles * p.n_j2_tiles * ceil_div(tiles, per);
             const double n = wg > 256 * 8 ? double(wg) / 256 : double(ceil_div(wg, 256));
             const double turns = n > double(8 * occ) ? n / double(occ) : double(ceil_div(int64_t(n + 0.999), occ));
-            const double cost = std::max(3.0 * turns, n) * double(per * nk + 4) * (1.0 + vx * double(ceil_div(tiles, per)));
+            const double cost = std::max(3.0 * turns, n) * double(per * nk + 4) + vx * double(ceil_div(tiles, per));
             if (c == 1 || cost < best) { best = cost; S = c; p.rows_per_split = per * rt.TM; }
         }
     }
@@ -2061,7 +2064,7 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
             reduced = true;
         }
         if (p.S > 1) {
-            p.rows_per_split = round_up(ceil_div(I2, p.S / 2), rt.TM);
+            p.rows_per_split = round_up(ceil_div(I2, p.S - 1), rt.TM);
         } else if (!one_split && p.KS > 1) {
             one_split = true;
         } else if (!tight) {
