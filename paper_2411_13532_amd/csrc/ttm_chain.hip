@@ -1965,13 +1965,25 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
     SlabTile rt = {};
     if (p.kern == SLAB_REG) {
         // all of J3 in one workgroup while two workgroups fit a compute unit
-        // (X is read once per j3 tile), in equal tiles past that
+        // (X is read once per j3 tile), in equal tiles past that; in float,
+        // bound by its products there, in the tiles that pad least (five blocks
+        // are taken as six), each counted as a block more for its reading of X: 143 x 148 x
+        // 80 -> 1, 60, 139 in float 42.7 us in two tiles of six, 29.6 in three
+        // of three
         const bool xf = xdt != TTM_BF16;
         const int most = math == TTM_MATH_F64 || (math == TTM_MATH_BF16X3 && xf) ? 4 : math == TTM_MATH_BF16 ? 8 : 6;
         p.CB = int(ceil_div(J3b, ceil_div(J3b, most)));
         if (p.CB == 5 || p.CB == 7) ++p.CB;
+        if (math == TTM_MATH_F32)
+            for (int c = 4; c >= 3; --c)
+                if (ceil_div(J3b, c) * (c + 1) < ceil_div(J3b, p.CB) * (p.CB + 1)) p.CB = c;
         p.cols = p.CB * 16;
-        jbmax = 8;
+        // j2 tiles of eight blocks; in float and double three of four where two
+        // of eight would be a quarter empty and a row is one chunk, which is soon
+        // formed again: 40 x 552 x 16 -> 2, 184, 80 in double 56.4 us in two of
+        // eight, 40.1 in three of four (longer rows, formed three times: 1.1 to
+        // 1.4 times the time)
+        jbmax = jbn > 8 && jbn <= 12 && I3 <= KC && !bf ? 4 : 8;
         tile();
         rt = slab_tile(math, xf, p.CB);
         p.WR = rt.WR;
