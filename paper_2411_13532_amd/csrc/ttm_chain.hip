@@ -639,34 +639,9 @@ __global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT
         if constexpr (CF::WALIAS) __syncthreads();             // the slot is filled again by the next chunk
     };
 
-    // chunks q, q + 1 and q + 2 (past the last one the last again: the fetches
-    // have no condition, so that the number of loads in flight, which the waits
-    // count, is the same on every path; for the same reason every step stores
-    // the next chunk and the steps come in pairs)
     int t = 0, kc = 0, t1 = 0, kc1 = 0, t2, kc2;
-    auto next = [&](int &tt, int &kk) {
-        if (kk + 1 < nk) { ++kk; return false; }
-        if (tt + 1 == ntiles) return false;
-        kk = 0;
-        ++tt;
-        return true;
-    };
-    fetch_c(0);
-    set_rows(0);
-    fetch_x(0, px[0]);
-    if (next(t1, kc1)) set_rows(t1);
-    fetch_x(kc1, px[1]);
-    t2 = t1; kc2 = kc1;
-    if (next(t2, kc2)) set_rows(t2);
-    store_c(0, 0);
-    store_x(0, 0, 0, px[0]);
-    __syncthreads();
-    auto step = [&](auto SLOT) __attribute__((always_inline)) {
+    auto products = [&](auto SLOT) __attribute__((always_inline)) {
         constexpr int S = decltype(SLOT)::value;
-        fetch_c(kc1);
-        if (kc == nk - 1) fetch_b(t);
-        fetch_x(kc2, px[S]);
-        __builtin_amdgcn_sched_barrier(0);
         if (row_begin + t * TM + wave * (16 * MB) < row_end) {
 #pragma unroll
             for (int kg = 0; kg < 2; ++kg) {
@@ -692,22 +667,69 @@ __global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT
                 }
             }
         }
-        store_c(1 - S, kc1);                // (after the last chunk: that chunk again, which nothing reads)
-        store_x(1 - S, t1, kc1, px[1 - S]);
-        __syncthreads();
-        if (kc == nk - 1) {
-            place_b(t);
-            mode2(t, S);
-        }
-        t = t1; kc = kc1;
-        t1 = t2; kc1 = kc2;
-        if (next(t2, kc2)) set_rows(t2);
     };
-    for (int64_t q = nq; q >= 2; q -= 2) {
-        step(std::integral_constant<int, 0>{});
-        step(std::integral_constant<int, 1>{});
+    // chunks q, q + 1 and q + 2 (past the last one the last again: the fetches
+    // have no condition, so that the number of loads in flight, which the waits
+    // count, is the same on every path; for the same reason every step stores
+    // the next chunk and the steps come in pairs)
+    auto next = [&](int &tt, int &kk) {
+        if (kk + 1 < nk) { ++kk; return false; }
+        if (tt + 1 == ntiles) return false;
+        kk = 0;
+        ++tt;
+        return true;
+    };
+    // One chunk in all, in the bf16 forms with one column block, where tensors
+    // of few columns have many such workgroups: nothing is fetched ahead (928 x
+    // 48 x 48 -> 7, 6, 7 in bf16 20.3 us with the chunk fetched three times, so
+    // 18.6).
+    constexpr bool SINGLE = !RAW && CB == 1;
+    if (SINGLE && nq == 1) {
+        fetch_c(0);
+        fetch_b(0);
+        set_rows(0);
+        fetch_x(0, px[0]);
+        store_c(0, 0);
+        store_x(0, 0, 0, px[0]);
+        __syncthreads();
+        products(std::integral_constant<int, 0>{});
+        __syncthreads();
+        mode2(0, 0);
+    } else {
+        fetch_c(0);
+        set_rows(0);
+        fetch_x(0, px[0]);
+        if (next(t1, kc1)) set_rows(t1);
+        fetch_x(kc1, px[1]);
+        t2 = t1; kc2 = kc1;
+        if (next(t2, kc2)) set_rows(t2);
+        store_c(0, 0);
+        store_x(0, 0, 0, px[0]);
+        __syncthreads();
+        auto step = [&](auto SLOT) __attribute__((always_inline)) {
+            constexpr int S = decltype(SLOT)::value;
+            fetch_c(kc1);
+            if (kc == nk - 1) fetch_b(t);
+            fetch_x(kc2, px[S]);
+            __builtin_amdgcn_sched_barrier(0);
+            products(SLOT);
+            store_c(1 - S, kc1);                // (after the last chunk: that chunk again, which nothing reads)
+            store_x(1 - S, t1, kc1, px[1 - S]);
+            __syncthreads();
+            if (kc == nk - 1) {
+                place_b(t);
+                mode2(t, S);
+            }
+            t = t1; kc = kc1;
+            t1 = t2; kc1 = kc2;
+            if (next(t2, kc2)) set_rows(t2);
+        };
+        for (int64_t q = nq; q >= 2; q -= 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        if (nq & 1) step(std::integral_constant<int, 0>{});
     }
-    if (nq & 1) step(std::integral_constant<int, 0>{});
 
     // V[i1][s * WR + w][j2][j3]: lane (g, c) register r of a block holds row acc_row(g, r), column c
     acc_t *Vp = static_cast<acc_t *>(a.V) + (i1 * a.P + s * WR) * a.J2pad * a.J3pad;
