@@ -111,4 +111,4 @@ def check(status: int, where: str) -> None:
 
 
 def shape(I, J) -> Shape:
-    return Shape(tuple(map(int, I)), tuple(map(int, J)))
+    return Shape((int(I[0]), int(I[1]), int(I[2])), (int(J[0]), int(J[1]), int(J[2])))

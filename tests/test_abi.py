@@ -324,3 +324,13 @@ def test_chain_takes_long_factors(lib, I, J, x, math):
     assert call(_lib.shape(I, J)) == _lib.TTM_ERR_HIP
     assert lib.ttm_chain_workspace_size(shp(I, J), x, _lib.MATH[math]) > 0
     assert call(_lib.shape(I, [j + (j > 3) for j in J])) == _lib.TTM_ERR_UNSUPPORTED
+
+
+def test_shape_takes_the_first_three_sizes():
+    """Any sequence of at least three numbers; fewer are an error, not zeros."""
+    import numpy as np
+    s = _lib.shape(np.array([3, 4, 5, 6]), [1, 2, 3, 4])
+    assert list(s.I) == [3, 4, 5] and list(s.J) == [1, 2, 3]
+    for I, J in (((3, 4), (1, 2, 3)), ((3, 4, 5), (1, 2))):
+        with pytest.raises(IndexError):
+            _lib.shape(I, J)
