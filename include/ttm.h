@@ -268,8 +268,8 @@ int ttm_batched_plan_config(const ttm_batched_plan *plan, int *out);
  * variant (0 to 4, as in ttm_batched_plan_config).  Rebuilds the
  * assignment of cuboids to waves (synchronising `stream`).  The results of
  * every shape are identical among the vector-unit variants (0-2) and among
- * the matrix-core variants (3, 4); the two families sum the terms of each
- * output in different orders (both to float rounding of the exact result).
+ * the matrix-core variants (3, 4); between the two families they may differ by
+ * float rounding.
  * TTM_ERR_INVALID_ARG for a shape outside these ranges, TTM_ERR_HIP. */
 int ttm_batched_plan_set_config(ttm_batched_plan *plan, int threads, int blocks_per_cu, int variant,
                                 void *stream);

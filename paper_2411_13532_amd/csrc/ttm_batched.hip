@@ -755,10 +755,14 @@ int ttm_batched_plan_create(int64_t count, const int64_t *dims_host, int dtype, 
     // Default launch shape: 4 waves per block, as many resident blocks as LDS
     // and registers allow, and of the variants the matrix-core one at four
     // waves per SIMD where every one of its waves has at least four cuboids to
-    // itself (cold, sizes 5..13: 20000 cuboids 85.5 us, the vector units at
-    // three waves 97.1; 2..8: 37.9, 45.4; 8 alone 48.8, 52.0; 13 alone 148, 166).
-    // With fewer its more numerous waves are the harder to balance (8328 of
-    // 7..13: 35.8, 34.5; 2773 of 8: 9.1, 7.8).
+    // itself: from there on it is ahead on a cold last-level cache whatever the
+    // sizes (20000 cuboids of 5..13 82.0 us, the vector units at three waves
+    // 93.5; 2..8 37.2, 44.2; 8 alone 47.6, 50.1; 13 alone 141, 154; 16 alone 251,
+    // 281; the one size behind is 11 alone, 98.5, 96.2) and, with the batch in the
+    // cache, for all but cubes of 7, 8, 10 or 11 (5..13 65.3, 70.5; 2..8 31.4,
+    // 36.0; but 8 alone 41.4, 37.4).  With fewer cuboids it depends on their
+    // sizes on either cache (warm, 2773 of 8 9.2, 7.9, of 16 40.2, 46.1; 8328 of
+    // 5..13 33.1, 32.7, of 13 56.8, 62.0; 700 of 13 13.7, 17.2).
     const bool mx = dtype == TTM_F32 && count >= int64_t(64) * p->cu_count;
     p->variant = mx && max_blocks_per_cu(p, 256, 4) >= 1 ? 4 : 1;
     p->threads = 256;

@@ -355,9 +355,12 @@ __device__ __forceinline__ void slab_mode2(typename MathTraits<MATH>::accv_t (&v
 // Bound by HBM in the bf16 forms, by the matrix cores in float and double on
 // full chips, by latency (a chunk's barrier, a fetch's trip) on small ones.
 // Measured, whole chains: 385 x 510 x 771 -> 48 x 50 x 70 in bf16, odd rows
-// read value by value with the waits of one chunk exposed: 287 us, now 115 us;
-// 181 x 210 x 155 -> 24 x 30 x 41 in double 59 us, now 45 us;
-// 332 x 409 x 232 -> 65 x 80 x 48 in double 568 us, now 224 us.
+// read value by value with the waits of one chunk exposed: 287 us, now 113 us;
+// 181 x 210 x 155 -> 24 x 30 x 41 in double 59 us, now 39.5 us;
+// 332 x 409 x 232 -> 65 x 80 x 48 in double 567 us, now 205 us.  With one column
+// block in plain bf16 and many short workgroups (i1 in the hundreds) the kernel
+// that handed W over in registers, at four and five workgroups a compute unit
+// where three fit now, was ahead: 888 x 16 x 64 -> 64 x 8 x 8 17.3 us, now 21.3.
 template <int MATH, typename XT, int CB, int JB>
 __global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT, float>::value, CB, JB)) k_slab(const SlabArgs a) {
     typedef SlabCfg<MATH, XT, CB> CF;
@@ -1718,10 +1721,10 @@ __global__ void __launch_bounds__(256) k_mode1(const Mode1Args a) {
 // registers, and their sums meet in LDS, in order.  Every load of a wave's
 // first groups is in flight at once and there is no split to sum in a second
 // launch.  Bound by the trips to V and A; 64^3 -> 16^3 in double: k_mode1 and
-// k_mode1_reduce 4.2 + 2.4 us and a launch, now 3.4 us; chains: 232 x 136 x 264
-// -> 104 x 43 x 80 in float (V 11 MB) 82, now 66 us; 512^3 -> 64 in float (V 16
-// MB) 218, now 215 us; at 1024 x 512 x 512 -> 128 in bf16x3 (V 64
-// MB) k_mode1 is ahead, 231 us against 278.
+// k_mode1_reduce 4.2 + 2.4 us and a launch, now 3.4 us; chains, k_mode1 first: 232
+// x 136 x 264 -> 104 x 43 x 80 in float (V 11 MB) 82 and 66 us, 512^3 -> 64 in
+// float (V 16 MB) 218 and 215; at 1024 x 512 x 512 -> 128 in bf16x3 (V 64 MB)
+// 231 and 278.
 template <int MATH, int MW, int NW>
 __global__ void __launch_bounds__(64 * NW) k_mode1_small(const Mode1Args a) {
     typedef Mode1Cfg<MATH> CF;
@@ -1906,18 +1909,23 @@ constexpr int64_t GRID_YZ = 65535;   // workgroups of a launch along y and z
 // (128-byte chunks) bf16 X with the bf16 forms and four column waves.
 // Automatic selection, whole chains measured on both sides (us):
 // * k_slab_lc where it applies and the row range of a workgroup holds at least
-//   one whole 256-row tile: bf16x3 1024 x 512 x 512 -> 128 228, k_slab 329;
-//   512 x 512 x 512 -> 100, 50, 100 113, 145; bf16 1024 x 512 x 512 -> 128 176,
-//   203.  (At 64 columns the two are within 7% either way.)
-// * k_slab_dma in float past 64 columns (256 x 512 x 512 -> 128: 229, k_slab
-//   246; 400 x 500 x 512 -> 100: 412, 462) and, in double, up to 32 where its
-//   128-row tiles are full (256 x 256 x 512 -> 16, 30, 12: 60, 65; -> 32: 74.6
-//   both).
-// * k_slab otherwise: float up to 64 columns (512^3 -> 64: 212.5, k_slab_dma
-//   213.3; 400 x 300 x 512 -> 64: 122, 131; 400 x 500 x 512 -> 16: 90, 111;
-//   256 x 512 x 512 -> 32: 66, 72), double (256^3 -> 64: 71, 86; 128 x 512 x
-//   512 -> 100, 120, 128: 256, 449; 64^3 -> 16: 15.7, 18.1), the bf16 forms where
-//   k_slab_lc does not apply (512^3 -> 32 bf16x3: 53, 76).
+//   one whole 256-row tile: bf16x3 1024 x 512 x 512 -> 128 231, k_slab 336;
+//   512 x 512 x 512 -> 100, 50, 100 110, 140; bf16 1024 x 512 x 512 -> 128 174,
+//   197.  (At 64 columns the two are within 7% either way.)
+// * k_slab_dma in float past 64 columns (256 x 512 x 512 -> 128: 227, k_slab
+//   249; 400 x 500 x 512 -> 100: 408, 462) and, in double, up to 32 where its
+//   128-row tiles are full (256 x 256 x 512 -> 16, 30, 12: 58.5, 64.1; -> 16, 30,
+//   32: 75.2, 71.4).  The line is drawn for full chips and 100 to 128 columns:
+//   up to 96, past 128 and on few workgroups k_slab is ahead there too (float
+//   256 x 512 x 512 -> 64, 64, 80 189, 157; 500 x 200 x 512 -> 20, 100, 144 391,
+//   270; 64 x 128 x 256 -> 20, 30, 128 30.6, 16.4; double 100 x 128 x 256 -> 16,
+//   30, 16 22.9, 16.6).
+// * k_slab otherwise: float up to 64 columns (512^3 -> 64: 200, k_slab_dma
+//   217; 400 x 300 x 512 -> 64: 115, 133; 400 x 500 x 512 -> 16: 89, 110;
+//   256 x 512 x 512 -> 32: 63, 70), double (256^3 -> 64: 70, 82; 128 x 512 x
+//   512 -> 100, 120, 128: 255, 452; 64^3 -> 16: 9.0, 11.5), the bf16 forms where
+//   k_slab_lc does not apply (512^3 -> 32 bf16x3: 52, 75; bf16 within 4% of each
+//   other; but 88 x 336 x 384 -> 24, 6, 72 bf16x3 26.9, 23.5).
 static SlabKernel pick_slab(const ttm_shape &s, int xdt, int math, const ChainPlan &p, int mode) {
     const int64_t I3 = s.I[2];
     const bool bf = math == TTM_MATH_BF16 || math == TTM_MATH_BF16X3;
@@ -1989,9 +1997,9 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         // all of J3 in one workgroup while two workgroups fit a compute unit
         // (X is read once per j3 tile), in equal tiles past that; in float,
         // bound by its products there, in the tiles that pad least (five blocks
-        // are taken as six), each counted as a block more for its reading of X: 143 x 148 x
-        // 80 -> 1, 60, 139 in float 42.7 us in two tiles of six, 29.6 in three
-        // of three
+        // are taken as six), each counted as a block more for its reading of X:
+        // 143 x 148 x 80 -> 1, 60, 139 in float 42.6 us in two tiles of six, 29.6
+        // in three of three
         const bool xf = xdt != TTM_BF16;
         const int most = math == TTM_MATH_F64 || (math == TTM_MATH_BF16X3 && xf) ? 4 : math == TTM_MATH_BF16 ? 8 : 6;
         p.CB = int(ceil_div(J3b, ceil_div(J3b, most)));
@@ -2019,8 +2027,8 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         // 140, 136, 39 in double to one split: 86.6 us, now 32.8.)
         // Counting rounds of workgroups alone (which took one split of 512 x 512 x
         // 500 -> 64 in float, and more than half of a second round idle) gave
-        // 242 us there, this 215; 424 x 392 x 48 -> 8 x 15 x 16 in double 40.5 us
-        // with its one split, 40.9 with this rule's two.
+        // 242 us there, this 204; 424 x 392 x 48 -> 8 x 15 x 16 in double 40.5 us
+        // with its one split, 39.9 with this rule's two.
         const int64_t nk = ceil_div(I3, KC), occ = std::min(4, 163840 / rt.lds);
         const double vx = 2.0 * double(I1) * double(p.J2pad) * double(p.J3pad) * double(p.acc_sz) /
                           (256.0 * double(rt.TM * std::min<int64_t>(I3, KC)) * double(dtype_size(xdt)));

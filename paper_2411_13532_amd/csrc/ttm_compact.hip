@@ -408,11 +408,12 @@ __global__ void __launch_bounds__(256) k_compact_rows_full(const CompactArgs a, 
 // again from it.  Where those are the whole fiber, one turn is enough: further
 // ones multiply its sum by 1 / (1 - (-rho)^n).  (Gone round as often as K points
 // take, fibers of 5 and 6 points paid for 40 dependent LDS reads: 267 x 5 x 1200
-// in double along mode 2 15.5 us, now 8.5; the exact sweeps, prepared, 7.8.)  The same backwards.  Each point is read once and
-// written once, whatever n.  Fibers too long for one block are taken in chunks
-// with K + 2 points more at either end, from zero there; the right-hand side is
-// zero at a chunk's two outermost points, whose neighbours it does not hold, so
-// that nothing of one end reaches the other.
+// in double along mode 2 15.5 us, now 8.5; the exact sweeps, prepared, 7.8.)  The
+// same backwards.  Each point is read once and written once, whatever n.
+// Fibers too long for one block are taken in chunks with K + 2 points more at
+// either end, from zero there; the right-hand side is zero at a chunk's two
+// outermost points, whose neighbours it does not hold, so that nothing of one
+// end reaches the other.
 // ---------------------------------------------------------------------------
 struct SegArgs {
     int64_t n, stride, nfib, i3, s12, groups;
