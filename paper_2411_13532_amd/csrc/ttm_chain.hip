@@ -113,6 +113,7 @@ template <typename XT, typename LT> struct XGroup;
 template <typename T> struct XGroup<T, T> {          // same type: one 16-byte load
     static constexpr int VE = 16 / sizeof(T), REGS = 4;
     V16 raw;
+    __device__ void clear() { raw = zero16(); }
     __device__ void load(const T *p) { raw.u = *reinterpret_cast<const u32x4_u *>(p); }
     __device__ void load_some(const T *p, int n) {
         T tmp[VE];
@@ -166,6 +167,7 @@ template <> struct XGroup<uint16_t, float> {        // bf16 X, float operands: 8
 template <> struct XGroup<float, uint16_t> {        // float X, bf16 operands: 32-byte load, split on store
     static constexpr int VE = 8, REGS = 8;
     V16 raw0, raw1;
+    __device__ void clear() { raw0 = raw1 = zero16(); }
     __device__ void load(const float *p) {
         raw0.u = *reinterpret_cast<const u32x4_u *>(p);
         raw1.u = *reinterpret_cast<const u32x4_u *>(p + 4);
@@ -749,6 +751,92 @@ __global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT
                     Vp[(w * a.J2pad + j2) * a.J3pad + col0 + (nb0 + j) * 16 + l16] = vacc[w][i][j][r];
                 }
             }
+}
+
+// ---------------------------------------------------------------------------
+// k_slab_rows: the same computation as k_slab, to the same bits, for plain bf16
+// and at most 16 columns j3 where many short workgroups take turns on the chip:
+// four waves of 32 rows each, X one chunk ahead through one register set, C's
+// fragments from L2, and W handed to the mode-2 step in the registers it was
+// summed in, so that four workgroups fit a compute unit where k_slab,
+// with two chunks ahead, C in LDS and W through LDS, has three.  Rows past I2
+// are not fetched.  Bound by the latency of its chunks' trips and by the number
+// of workgroups that share them: 769 x 10 x 269 -> 1, 5, 2, the whole chain, 29.9
+// us with k_slab, 18.4 with this one; 888 x 16 x 64 -> 64, 8, 8 21.5 and 19.3.
+// ---------------------------------------------------------------------------
+template <typename XT, int JB>
+__global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(const SlabArgs a) {
+    typedef MathTraits<M_BF16> TR;
+    constexpr int VE = TR::VE, KG = TR::KG, KC = 2 * KG, GROUPS = SLAB_TM * 8 / SLAB_THREADS, TILE = SLAB_TM * SLAB_ROWB;
+    __shared__ __align__(16) unsigned char tile[2][TILE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int64_t i1 = blockIdx.x / a.S;
+    const int s = int(blockIdx.x % a.S);
+    const int64_t row_begin = int64_t(s) * a.rows_per_split;
+    const int64_t row_end = a.I2 < row_begin + a.rows_per_split ? a.I2 : row_begin + a.rows_per_split;
+    const int jbase = int(blockIdx.z) * JB;
+    const XT *Xs = static_cast<const XT *>(a.X) + i1 * a.I2 * a.I3;
+    const uint16_t *Ch = static_cast<const uint16_t *>(a.Chi) + l16 * a.ldc;
+    const int nk = int(ceil_div(a.I3, KC)), ntiles = int(ceil_div(row_end - row_begin, SLAB_TM));
+    f32x4 vacc[JB][1], wacc[2][1];
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) vacc[jb][0] = zero_accv<f32x4>();
+    XGroup<XT, uint16_t> x[GROUPS];
+    const int gr = tid >> 3, gp = tid & 7;             // row and 16-byte piece of a thread's first group
+    auto fetch = [&](int t, int kc) __attribute__((always_inline)) {
+        const int64_t k = int64_t(kc) * KC + gp * VE, kleft = a.I3 - k;
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j) {
+            const int64_t row = row_begin + int64_t(t) * SLAB_TM + gr + 32 * j;
+            const XT *p = Xs + row * a.I3 + k;
+            if (row < row_end && kleft >= VE) x[j].load(p);
+            else if (row < row_end && kleft > 0) x[j].load_some(p, int(kleft));
+            else x[j].clear();
+        }
+    };
+    auto store = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j) x[j].store(tile[buf] + (gr + 32 * j) * SLAB_ROWB + gp * 16, nullptr);
+    };
+    fetch(0, 0);
+    store(0);
+    __syncthreads();
+    int buf = 0;
+    for (int t = 0; t < ntiles; ++t) {
+        wacc[0][0] = wacc[1][0] = zero_accv<f32x4>();
+        const int64_t wrow0 = row_begin + int64_t(t) * SLAB_TM + wave * 32;
+        for (int kc = 0; kc < nk; ++kc, buf ^= 1) {
+            const bool last = kc + 1 == nk, more = !last || t + 1 < ntiles;
+            if (more) fetch(last ? t + 1 : t, last ? 0 : kc + 1);
+            if (wrow0 < row_end)
+#pragma unroll
+                for (int kg = 0; kg < 2; ++kg) {
+                    const V16 c = ld16(Ch + int64_t(kc) * KC + kg * KG + g * VE);
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb) {
+                        V16 r;
+                        r.u = *reinterpret_cast<const u32x4 *>(tile[buf] + (wave * 32 + mb * 16 + l16) * SLAB_ROWB + kg * 64 + g * 16);
+                        mma_kgroup<M_BF16>(wacc[mb][0], r, c);
+                    }
+                }
+            if (more) store(buf ^ 1);
+            __syncthreads();
+        }
+        if (wrow0 >= row_end) continue;
+        if (wrow0 + 32 > row_end)                      // (zeros times an infinite entry of C are NaN)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (wrow0 + mb * 16 + TR::acc_row(g, r) >= row_end) wacc[mb][0][r] = 0.f;
+        slab_mode2<M_BF16, 2, 1, JB>(vacc, wacc, a, jbase, wrow0, l16, g);
+    }
+    float *Vp = static_cast<float *>(a.V) + (i1 * a.P + s * 4 + wave) * a.J2pad * a.J3pad;
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Vp[((jbase + jb) * 16 + TR::acc_row(g, r)) * a.J3pad + l16] = vacc[jb][0][r];
 }
 
 // ---------------------------------------------------------------------------
@@ -1870,6 +1958,7 @@ struct ChainPlan {
     int WC, NBW, WR, JB, MBK, m1_MW, m1_NW;
     bool m1_small;                // mode 1 by k_mode1_small
     int CB;                       // SLAB_REG: 16-column blocks of a workgroup
+    bool rows;                    // SLAB_REG: k_slab_rows in place of k_slab
     int64_t cols;                 // j3 columns per workgroup
     int64_t J3pad, J2pad, J1pad;
     int64_t n_j3_tiles, n_j2_tiles, n_m1_tiles;
@@ -2017,6 +2106,16 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         tile();
         rt = slab_tile(math, xf, p.CB);
         p.WR = rt.WR;
+        // k_slab_rows while a workgroup has few chunks, or half of its rows and
+        // more are past I2 and are not fetched; not for single chunks that fill the
+        // chip at most once, nor for long walks, which want two chunks ahead.  Plain
+        // bf16, k_slab and k_slab_rows: 981 x 8 x 331 -> 32, 2, 1 35.0 and 20.7 us,
+        // 896 x 91 x 49 -> 88, 8, 8 21.2 and 19.3, 544 x 248 x 206 -> 48, 6, 14 34.1
+        // and 35.0; past the lines 832 x 869 x 600 -> 1, 1, 8 221 and 240, 53 x 389 x
+        // 600 -> 2, 13, 14 of float 20.2 and 23.2, 16 x 22 x 18 -> 2, 1, 1 9.9 and 10.2
+        const int64_t walk = ceil_div(std::min(I2, p.rows_per_split), rt.TM) * ceil_div(I3, KC);
+        p.rows = mode == 0 && math == TTM_MATH_BF16 && J3 <= 16 && (walk <= 6 || 2 * I2 <= rt.TM) &&
+                 (walk > 1 || I1 * ceil_div(I2, p.rows_per_split) * p.n_j2_tiles > 256);
         // row splits: a compute unit's workgroups n take n chunk times where
         // they fill it and about three where one waits out its chunk's trips
         // alone, for as many chunks as a workgroup has and four more for its
@@ -2161,8 +2260,21 @@ static int dispatch_slab_reg_jb(const ChainPlan &p, const SlabArgs &a, hipStream
     }
 }
 
+template <typename XT>
+static int dispatch_slab_rows(const ChainPlan &p, const SlabArgs &a, hipStream_t st) {
+    dim3 grid(unsigned(a.I1 * a.S), 1, unsigned(p.n_j2_tiles));
+    return launch("ttm_slab", st, [&] {
+        auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(SLAB_THREADS), 0, st, a); };
+        if (p.JB == 1) go(k_slab_rows<XT, 1>);
+        else if (p.JB == 2) go(k_slab_rows<XT, 2>);
+        else if (p.JB == 4) go(k_slab_rows<XT, 4>);
+        else go(k_slab_rows<XT, 8>);
+    });
+}
+
 template <int MATH, typename XT>
 static int dispatch_slab_reg(const ChainPlan &p, const SlabArgs &a, hipStream_t st) {
+    if constexpr (MATH == M_BF16) if (p.rows) return dispatch_slab_rows<XT>(p, a, st);
     switch (p.CB) {
         case 1: return dispatch_slab_reg_jb<MATH, XT, 1>(p, a, st);
         case 2: return dispatch_slab_reg_jb<MATH, XT, 2>(p, a, st);
