@@ -140,6 +140,7 @@ template <typename T> struct XGroup<T, T> {          // same type: one 16-byte l
 template <> struct XGroup<uint16_t, float> {        // bf16 X, float operands: 8-byte load
     static constexpr int VE = 4, REGS = 2;
     u32x2 raw;
+    __device__ void clear() { raw = u32x2{0u, 0u}; }
     __device__ void load(const uint16_t *p) { raw = *reinterpret_cast<const u32x2_u *>(p); }
     __device__ void load_some(const uint16_t *p, int n) {
         uint32_t h[4];
@@ -754,21 +755,30 @@ __global__ void __launch_bounds__(SLAB_THREADS, slab_waves(MATH, std::is_same<XT
 }
 
 // ---------------------------------------------------------------------------
-// k_slab_rows: the same computation as k_slab, to the same bits, for plain bf16
-// and at most 16 columns j3 where many short workgroups take turns on the chip:
-// four waves of 32 rows each, X one chunk ahead through one register set, C's
-// fragments from L2, and W handed to the mode-2 step in the registers it was
-// summed in, so that four workgroups fit a compute unit where k_slab,
-// with two chunks ahead, C in LDS and W through LDS, has three.  Rows past I2
-// are not fetched.  Bound by the latency of its chunks' trips and by the number
-// of workgroups that share them: 769 x 10 x 269 -> 1, 5, 2, the whole chain, 29.9
-// us with k_slab, 18.4 with this one; 888 x 16 x 64 -> 64, 8, 8 21.5 and 19.3.
+// k_slab_rows: the same computation as k_slab for at most 16 columns j3 and
+// short walks, where a workgroup's time is not its bytes: four waves of 32 rows
+// each, X one chunk ahead through one register set, W handed to the mode-2 step
+// in the registers it was summed in (no W tile, no barriers for it), four
+// workgroups a compute unit.  Rows past I2 are not fetched.  Float and double:
+// all of C in LDS from the start, B read where it is, the waves' shares of V
+// added at the end.  Plain bf16: C's fragments from L2, a partial of V per wave,
+// as in k_slab and to the same bits.  Bound by the latency of the chunks' trips
+// and by the number of workgroups that share them.  The whole chain, k_slab and
+// this one: 769 x 10 x 269 -> 1, 5, 2 in bf16 29.9 and 18.4 us; 941 x 928 x 16 ->
+// 1, 3, 1 in float 54.5 and 29.2; 808 x 635 x 6 -> 35, 8, 2 in double 70 and 35;
+// 424 x 392 x 48 -> 8, 15, 16 in double 39.9 and 24.9.
 // ---------------------------------------------------------------------------
-template <typename XT, int JB>
+constexpr int slab_rows_lds(int64_t nk) { return (2 * SLAB_TM + 16 * int(nk)) * SLAB_ROWB; }   // X twice, all of C (float and double)
+template <int MATH, typename XT, int JB>
 __global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(const SlabArgs a) {
-    typedef MathTraits<M_BF16> TR;
+    typedef MathTraits<MATH> TR;
+    typedef typename TR::lds_t LT;
+    typedef typename TR::fac_t FT;
+    typedef typename TR::acc_t acc_t;
+    typedef typename TR::accv_t accv;
+    constexpr bool RAW = MATH != M_BF16;
     constexpr int VE = TR::VE, KG = TR::KG, KC = 2 * KG, GROUPS = SLAB_TM * 8 / SLAB_THREADS, TILE = SLAB_TM * SLAB_ROWB;
-    __shared__ __align__(16) unsigned char tile[2][TILE];
+    extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int64_t i1 = blockIdx.x / a.S;
@@ -777,12 +787,12 @@ __global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(con
     const int64_t row_end = a.I2 < row_begin + a.rows_per_split ? a.I2 : row_begin + a.rows_per_split;
     const int jbase = int(blockIdx.z) * JB;
     const XT *Xs = static_cast<const XT *>(a.X) + i1 * a.I2 * a.I3;
-    const uint16_t *Ch = static_cast<const uint16_t *>(a.Chi) + l16 * a.ldc;
+    const FT *Ch = static_cast<const FT *>(a.Chi), *Bh = static_cast<const FT *>(a.Bhi);
     const int nk = int(ceil_div(a.I3, KC)), ntiles = int(ceil_div(row_end - row_begin, SLAB_TM));
-    f32x4 vacc[JB][1], wacc[2][1];
+    accv vacc[JB][1], wacc[2][1];
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb) vacc[jb][0] = zero_accv<f32x4>();
-    XGroup<XT, uint16_t> x[GROUPS];
+    for (int jb = 0; jb < JB; ++jb) vacc[jb][0] = zero_accv<accv>();
+    XGroup<XT, LT> x[GROUPS];
     const int gr = tid >> 3, gp = tid & 7;             // row and 16-byte piece of a thread's first group
     auto fetch = [&](int t, int kc) __attribute__((always_inline)) {
         const int64_t k = int64_t(kc) * KC + gp * VE, kleft = a.I3 - k;
@@ -797,14 +807,21 @@ __global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(con
     };
     auto store = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < GROUPS; ++j) x[j].store(tile[buf] + (gr + 32 * j) * SLAB_ROWB + gp * 16, nullptr);
+        for (int j = 0; j < GROUPS; ++j) x[j].store(smem + buf * TILE + (gr + 32 * j) * SLAB_ROWB + gp * 16, nullptr);
     };
     fetch(0, 0);
+    if constexpr (RAW)                                 // C, zero past its ends
+        for (int i = tid; i < nk * 128; i += SLAB_THREADS) {
+            const int row = i >> 3 & 15, k = (i >> 7) * KC + (i & 7) * VE;
+            XGroup<FT, FT> c;
+            c.load_some(Ch + row * a.I3 + k, row < a.J3 && k < a.I3 ? int(a.I3 - k) : 0);
+            c.store(smem + 2 * TILE + ((i >> 7) * 16 + row) * SLAB_ROWB + (i & 7) * 16, nullptr);
+        }
     store(0);
     __syncthreads();
     int buf = 0;
     for (int t = 0; t < ntiles; ++t) {
-        wacc[0][0] = wacc[1][0] = zero_accv<f32x4>();
+        wacc[0][0] = wacc[1][0] = zero_accv<accv>();
         const int64_t wrow0 = row_begin + int64_t(t) * SLAB_TM + wave * 32;
         for (int kc = 0; kc < nk; ++kc, buf ^= 1) {
             const bool last = kc + 1 == nk, more = !last || t + 1 < ntiles;
@@ -812,13 +829,11 @@ __global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(con
             if (wrow0 < row_end)
 #pragma unroll
                 for (int kg = 0; kg < 2; ++kg) {
-                    const V16 c = ld16(Ch + int64_t(kc) * KC + kg * KG + g * VE);
+                    const V16 c = RAW ? ld16(smem + 2 * TILE + (kc * 16 + l16) * SLAB_ROWB + kg * 64 + g * 16)
+                                      : ld16(Ch + l16 * a.ldc + int64_t(kc) * KC + kg * KG + g * VE);
 #pragma unroll
-                    for (int mb = 0; mb < 2; ++mb) {
-                        V16 r;
-                        r.u = *reinterpret_cast<const u32x4 *>(tile[buf] + (wave * 32 + mb * 16 + l16) * SLAB_ROWB + kg * 64 + g * 16);
-                        mma_kgroup<M_BF16>(wacc[mb][0], r, c);
-                    }
+                    for (int mb = 0; mb < 2; ++mb)
+                        mma_kgroup<MATH>(wacc[mb][0], ld16(smem + buf * TILE + (wave * 32 + mb * 16 + l16) * SLAB_ROWB + kg * 64 + g * 16), c);
                 }
             if (more) store(buf ^ 1);
             __syncthreads();
@@ -829,14 +844,51 @@ __global__ void __launch_bounds__(SLAB_THREADS, JB == 8 ? 3 : 4) k_slab_rows(con
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (wrow0 + mb * 16 + TR::acc_row(g, r) >= row_end) wacc[mb][0][r] = 0.f;
-        slab_mode2<M_BF16, 2, 1, JB>(vacc, wacc, a, jbase, wrow0, l16, g);
+                    if (wrow0 + mb * 16 + TR::acc_row(g, r) >= row_end) wacc[mb][0][r] = 0;
+        if constexpr (RAW) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                const int64_t w0 = wrow0 + mb * 16, n = a.I2 - w0;
+#pragma unroll
+                for (int jb = 0; jb < JB; ++jb) {
+                    const int64_t j = (jbase + jb) * 16 + l16;
+                    const FT *b = Bh + (j < a.J2 ? j : a.J2 - 1) * a.I2 + w0;
+                    FT bv[4];
+                    if (MATH == M_F32 && n >= 16) __builtin_memcpy(bv, reinterpret_cast<const u32x4_u *>(b + 4 * g), 16);
+                    else
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) bv[r] = TR::acc_row(g, r) < n ? b[TR::acc_row(g, r)] : FT(0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if constexpr (MATH == M_F32) vacc[jb][0] = mfma_f32(bv[r], wacc[mb][0][r], vacc[jb][0]);
+                        else vacc[jb][0] = mfma_f64(bv[r], wacc[mb][0][r], vacc[jb][0]);
+                    }
+                }
+            }
+        } else {
+            slab_mode2<MATH, 2, 1, JB>(vacc, wacc, a, jbase, wrow0, l16, g);
+        }
     }
-    float *Vp = static_cast<float *>(a.V) + (i1 * a.P + s * 4 + wave) * a.J2pad * a.J3pad;
+    acc_t *Vp = static_cast<acc_t *>(a.V) + (i1 * a.P + (RAW ? s : s * 4 + wave)) * a.J2pad * a.J3pad + int64_t(jbase) * 16 * a.J3pad;
+    if constexpr (RAW) {                               // the waves' shares, in order, where X was
+        static_assert(4 * JB * 256 * sizeof(acc_t) <= 2 * TILE, "");
+        acc_t *sum = reinterpret_cast<acc_t *>(smem);
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb)
+        for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Vp[((jbase + jb) * 16 + TR::acc_row(g, r)) * a.J3pad + l16] = vacc[jb][0][r];
+            for (int r = 0; r < 4; ++r) sum[(wave * JB + jb) * 256 + TR::acc_row(g, r) * 16 + l16] = vacc[jb][0][r];
+        __syncthreads();
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) {
+            const acc_t *v = sum + jb * 256 + tid;
+            Vp[(jb * 16 + (tid >> 4)) * a.J3pad + (tid & 15)] = (v[0] + v[JB * 256]) + (v[2 * JB * 256] + v[3 * JB * 256]);
+        }
+    } else {
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Vp[(jb * 16 + TR::acc_row(g, r)) * a.J3pad + l16] = vacc[jb][0][r];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2106,16 +2158,22 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         tile();
         rt = slab_tile(math, xf, p.CB);
         p.WR = rt.WR;
-        // k_slab_rows while a workgroup has few chunks, or half of its rows and
-        // more are past I2 and are not fetched; not for single chunks that fill the
-        // chip at most once, nor for long walks, which want two chunks ahead.  Plain
-        // bf16, k_slab and k_slab_rows: 981 x 8 x 331 -> 32, 2, 1 35.0 and 20.7 us,
-        // 896 x 91 x 49 -> 88, 8, 8 21.2 and 19.3, 544 x 248 x 206 -> 48, 6, 14 34.1
-        // and 35.0; past the lines 832 x 869 x 600 -> 1, 1, 8 221 and 240, 53 x 389 x
+        // k_slab_rows for at most 16 columns j3.  In float and double while J2 is
+        // at most 32 (past that k_slab deals the blocks of j2 to its waves: 80 x 8
+        // x 96 -> 6, 85, 2 of bf16 in float 9.6 us, here 11.4) and a row at most
+        // five chunks (longer rows want two chunks ahead: 800 x 33 x 184 -> 3, 1, 2
+        // 19.9 and 22.2).  In plain bf16 while a workgroup has few chunks, or half
+        // of its rows and more are past I2 and are not fetched; not for single
+        // chunks that fill the chip at most once, nor for long walks: 981 x 8 x 331 -> 32, 2, 1 35.0 and 20.7 us, 896 x
+        // 91 x 49 -> 88, 8, 8 21.2 and 19.3, 544 x 248 x 206 -> 48, 6, 14 34.1 and
+        // 35.0; past the lines 832 x 869 x 600 -> 1, 1, 8 221 and 240, 53 x 389 x
         // 600 -> 2, 13, 14 of float 20.2 and 23.2, 16 x 22 x 18 -> 2, 1, 1 9.9 and 10.2
-        const int64_t walk = ceil_div(std::min(I2, p.rows_per_split), rt.TM) * ceil_div(I3, KC);
-        p.rows = mode == 0 && math == TTM_MATH_BF16 && J3 <= 16 && (walk <= 6 || 2 * I2 <= rt.TM) &&
-                 (walk > 1 || I1 * ceil_div(I2, p.rows_per_split) * p.n_j2_tiles > 256);
+        const int64_t nk = ceil_div(I3, KC), walk = ceil_div(std::min(I2, p.rows_per_split), SLAB_TM) * nk;
+        p.rows = mode == 0 && J3 <= 16 && !p.split &&
+                 (bf ? (walk <= 6 || 2 * I2 <= SLAB_TM) &&
+                           (walk > 1 || I1 * ceil_div(I2, p.rows_per_split) * p.n_j2_tiles > 256)
+                     : p.JB <= 2 && nk <= 5);
+        const int64_t TM = p.rows ? SLAB_TM : rt.TM;
         // row splits: a compute unit's workgroups n take n chunk times where
         // they fill it and about three where one waits out its chunk's trips
         // alone, for as many chunks as a workgroup has and four more for its
@@ -2128,17 +2186,17 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
         // 500 -> 64 in float, and more than half of a second round idle) gave
         // 242 us there, this 204; 424 x 392 x 48 -> 8 x 15 x 16 in double 40.5 us
         // with its one split, 39.9 with this rule's two.
-        const int64_t nk = ceil_div(I3, KC), occ = std::min(4, 163840 / rt.lds);
+        const int64_t occ = std::min(4, 163840 / (p.rows ? slab_rows_lds(nk) : rt.lds));
         const double vx = 2.0 * double(I1) * double(p.J2pad) * double(p.J3pad) * double(p.acc_sz) /
-                          (256.0 * double(rt.TM * std::min<int64_t>(I3, KC)) * double(dtype_size(xdt)));
+                          (256.0 * double(TM * std::min<int64_t>(I3, KC)) * double(dtype_size(xdt)));
         double best = 0;
-        const int64_t tiles = ceil_div(I2, rt.TM);
+        const int64_t tiles = ceil_div(I2, TM);
         for (int64_t c = 1; c <= std::min<int64_t>(tiles, 64) && math != TTM_MATH_BF16; c += c < 8 ? 1 : 8) {
             const int64_t per = ceil_div(tiles, c), wg = I1 * p.n_j3_tiles * p.n_j2_tiles * ceil_div(tiles, per);
             const double n = wg > 256 * 8 ? double(wg) / 256 : double(ceil_div(wg, 256));
             const double turns = n > double(8 * occ) ? n / double(occ) : double(ceil_div(int64_t(n + 0.999), occ));
             const double cost = std::max(3.0 * turns, n) * double(per * nk + 4) + vx * double(ceil_div(tiles, per));
-            if (c == 1 || cost < best) { best = cost; S = c; p.rows_per_split = per * rt.TM; }
+            if (c == 1 || cost < best) { best = cost; S = c; p.rows_per_split = per * TM; }
         }
     }
 
@@ -2205,7 +2263,7 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
             reduced = true;
         }
         if (p.S > 1) {
-            p.rows_per_split = round_up(ceil_div(I2, p.S - 1), rt.TM);
+            p.rows_per_split = round_up(ceil_div(I2, p.S - 1), p.rows ? SLAB_TM : rt.TM);
         } else if (!one_split && p.KS > 1) {
             one_split = true;
         } else if (!tight) {
@@ -2215,7 +2273,7 @@ static bool make_plan(const ttm_shape &s, int xdt, int math, int mode, ChainPlan
             jbmax = 4;
             tile();
             rt = slab_tile(math, xdt != TTM_BF16, p.CB);
-            p.rows_per_split = round_up(I2, rt.TM);
+            p.rows_per_split = round_up(I2, p.rows ? SLAB_TM : rt.TM);
         } else {
             p = first;
             break;
@@ -2260,21 +2318,24 @@ static int dispatch_slab_reg_jb(const ChainPlan &p, const SlabArgs &a, hipStream
     }
 }
 
-template <typename XT>
+template <int MATH, typename XT>
 static int dispatch_slab_rows(const ChainPlan &p, const SlabArgs &a, hipStream_t st) {
-    dim3 grid(unsigned(a.I1 * a.S), 1, unsigned(p.n_j2_tiles));
+    const dim3 grid(unsigned(a.I1 * a.S), 1, unsigned(p.n_j2_tiles));
+    const int lds = slab_rows_lds(MATH == M_BF16 ? 0 : ceil_div(a.I3, 2 * MathTraits<MATH>::KG));
     return launch("ttm_slab", st, [&] {
-        auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(SLAB_THREADS), 0, st, a); };
-        if (p.JB == 1) go(k_slab_rows<XT, 1>);
-        else if (p.JB == 2) go(k_slab_rows<XT, 2>);
-        else if (p.JB == 4) go(k_slab_rows<XT, 4>);
-        else go(k_slab_rows<XT, 8>);
+        auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(SLAB_THREADS), lds, st, a); };
+        if (p.JB == 1) return go(k_slab_rows<MATH, XT, 1>);
+        if (p.JB == 2) return go(k_slab_rows<MATH, XT, 2>);
+        if constexpr (MATH == M_BF16) {
+            if (p.JB == 4) return go(k_slab_rows<MATH, XT, 4>);
+            return go(k_slab_rows<MATH, XT, 8>);
+        }
     });
 }
 
 template <int MATH, typename XT>
 static int dispatch_slab_reg(const ChainPlan &p, const SlabArgs &a, hipStream_t st) {
-    if constexpr (MATH == M_BF16) if (p.rows) return dispatch_slab_rows<XT>(p, a, st);
+    if constexpr (MATH != M_BF16X3) if (p.rows) return dispatch_slab_rows<MATH, XT>(p, a, st);
     switch (p.CB) {
         case 1: return dispatch_slab_reg_jb<MATH, XT, 1>(p, a, st);
         case 2: return dispatch_slab_reg_jb<MATH, XT, 2>(p, a, st);
@@ -2536,13 +2597,15 @@ size_t ttm_chain_workspace_size(const ttm_shape *s, int x_dtype, int math) {
     const int f = math == TTM_MATH_F64 ? TTM_F64 : TTM_F32;
     if (!combo_ok(x_dtype, f, f, math)) return 0;
     // enough for every kernel selection, which may change between the query
-    // and the call: the register-staged kernel's plan and the direct ones'
-    // (which share theirs)
+    // and the call: the register-staged kernel's plan, k_slab_rows' (its row
+    // splits are its own) and the direct ones' (which share theirs)
     ChainPlan p, d;
     if (!make_plan(*s, x_dtype, math, 1, p)) return 0;
+    size_t total = p.total;
+    if (make_plan(*s, x_dtype, math, 0, d)) total = std::max(total, d.total);
     for (int mode : {2, 3})
-        if (make_plan(*s, x_dtype, math, mode, d) && d.kern != SLAB_REG) return std::max(p.total, d.total);
-    return p.total;
+        if (make_plan(*s, x_dtype, math, mode, d) && d.kern != SLAB_REG) return std::max(total, d.total);
+    return total;
 }
 
 int ttm_chain(const ttm_shape *s, const void *X, int x_dtype, const void *A, const void *B, const void *C,

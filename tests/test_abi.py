@@ -326,6 +326,31 @@ def test_chain_takes_long_factors(lib, I, J, x, math):
     assert call(_lib.shape(I, [j + (j > 3) for j in J])) == _lib.TTM_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("x,math", [(_lib.TTM_F64, "f64"), (_lib.TTM_F32, "f32"), (_lib.TTM_BF16, "f32"), (_lib.TTM_BF16, "bf16"),
+                                    (_lib.TTM_F32, "bf16"), (_lib.TTM_BF16, "bf16x3"), (_lib.TTM_F32, "bf16x3")])
+def test_workspace_query_is_enough_for_the_call(lib, x, math):
+    """Under every kernel selection, over drawn shapes and one whose narrow
+    kernel takes more row splits than the one it replaces."""
+    import random
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up addresses: only where nothing can be launched")
+    r = random.Random(13)
+    f = _lib.TTM_F64 if math == "f64" else _lib.TTM_F32
+    fake = [(k + 1) << 54 for k in range(6)]
+    shapes = [((952, 135, 138), (16, 2, 2))]
+    shapes += [([int(2 ** r.uniform(0, 10)) for _ in range(3)], [int(2 ** r.uniform(0, 7.5)) for _ in range(3)]) for _ in range(400)]
+    try:
+        for I, J in shapes:
+            size = lib.ttm_chain_workspace_size(shp(I, J), x, _lib.MATH[math])
+            for mode in (0, 1, 2, 3):
+                assert lib.ttm_set_slab_kernel(mode) == 0
+                rc = lib.ttm_chain(shp(I, J), fake[0], x, fake[1], fake[2], fake[3], f, fake[4], f, _lib.MATH[math], fake[5], size, None)
+                assert rc == _lib.TTM_ERR_HIP, (I, J, mode)
+    finally:
+        lib.ttm_set_slab_kernel(0)
+
+
 def test_shape_takes_the_first_three_sizes():
     """Any sequence of at least three numbers; fewer are an error, not zeros."""
     import numpy as np
